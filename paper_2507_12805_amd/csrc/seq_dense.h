@@ -350,6 +350,7 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(Gemm gd, Gemm gw, int
   float in[2][8];
   if constexpr (!VIRT) t.in_mem(0, in);
   // the first four workgroups' waves take one tile of 16 bias columns each
+  // (so D is at least 256: dense_ok)
   const bool bias_wg = tx < 4;
   f32x4_t accb = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
   auto step = [&](auto last_c, int j0) {

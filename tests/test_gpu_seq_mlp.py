@@ -184,6 +184,30 @@ def test_streamed_layers_match_general(gpu, bs, t, E, opt, blocks):
     assert np.array_equal(gpu.decompress(blob).cpu().numpy(), a)
 
 
+@pytest.mark.parametrize("hidden,t,k,opt,blocks", [([128, 256], 4, 3, "adam", 256), ([192, 256], 4, 3, "sgd", 171),
+                                                   ([64, 256], 4, 3, "adam", 512), ([256], 3, 3, "adam", 171),
+                                                   ([128], 4, 4, "adam", 256), ([128, 192], 4, 4, "sgd", 256)])
+def test_layers_of_few_inputs_match_general(gpu, hidden, t, k, opt, blocks):
+    """256-wide layers of 64, 128 and 192 inputs (a hidden layer; the first
+    layer at t E = 192; the logits of (2,4)-mers) in as many blocks as fill
+    512 tiles of 64 rows: the first and last blocks' streams equal their
+    single-block runs, on the general products."""
+    bs, s = 16, 2
+    L = t + 12
+    n1 = s * bs * L + k - s
+    cfg = model_small(s=s, k=k, t=t, E=64, hidden=hidden, bs=bs, optimizer=opt, lr=0.05 if opt == "sgd" else 1e-2,
+                      precision="bf16", n_blocks=blocks)
+    a = synth.generate(synth.Recipe(n=blocks * n1, order=3, seed=51))
+    blob = gpu.compress(cfg, _cuda(a))
+    assert blob[5] == 7
+    got = cbf.parse(blob)["blocks"]
+    for b in (0, blocks - 1):
+        tok = gpu.encode_skmer(_cuda(a[b * n1:(b + 1) * n1]), s, k)[:bs * L]
+        _, _, streams = gpu.model_trace(dict(cfg, n_blocks=1), tok, streams=True)
+        assert b"".join(got[b]["streams"]) == streams
+    assert np.array_equal(gpu.decompress(blob).cpu().numpy(), a)
+
+
 @pytest.mark.parametrize("rows", [1, 16, 63, 64, 65, 127, 128])
 @pytest.mark.parametrize("t", [3, 16, 64])
 def test_first_layer_op_matches_general(gpu, rows, t):

@@ -230,3 +230,21 @@ def test_coding_rows_in_groups(gpu, bs, k):
     want = torch.softmax(gpu.dm_forward(cfg, w[:-1].contiguous(), ctx).double(), -1)
     assert P[0].shape == want.shape
     assert (P[0].double() - want).abs().max().item() <= 1e-6
+
+
+@pytest.mark.parametrize("A,F,heads,bs,blocks", [(256, 128, 4, 16, 256), (128, 256, 4, 16, 256)])
+def test_wide_layers_match_general(gpu, A, F, heads, bs, blocks):
+    """256-wide layers of 128 inputs in enough blocks to fill 512 tiles of 64
+    rows: the first and last blocks' streams equal their single-block
+    runs."""
+    cfg = _tf(t=4, E=64, A=A, F=F, heads=heads, bs=bs, precision="bf16", optimizer="adam", lr=0.003, n_blocks=blocks)
+    L = cfg["t"] + 8
+    n1 = 3 * bs * L
+    a = _dna(blocks * n1, 15)
+    blob = gpu.compress(cfg, _cuda(a))
+    got = cbf.parse(blob)["blocks"]
+    for b in (0, blocks - 1):
+        tok = gpu.encode_skmer(_cuda(a[b * n1:(b + 1) * n1]), 3, 3)[:bs * L]
+        _, _, streams = gpu.model_trace(dict(cfg, n_blocks=1), tok, streams=True)
+        assert b"".join(got[b]["streams"]) == streams
+    assert np.array_equal(gpu.decompress(blob).cpu().numpy(), a)
