@@ -10,8 +10,9 @@
 // a weight tile through LDS once per 64-row tile of the other operand and
 // once more for the update; here the row operand is what passes through LDS.
 //
-// Values: the k-steps of every output element, the slices of a split and
-// the order they are added in are gemm_kernel's.  A product may be computed
+// Values: the k-steps of every output element are gemm_kernel's, and where a
+// kernel takes a product that is split over K, the slices and the order they
+// are added in (the layer's backward takes none).  A product may be computed
 // transposed (operands exchanged): the matrix cores multiply and add the
 // same pairs in the same slots, so the bits are the same.
 #pragma once

@@ -1376,12 +1376,15 @@ Gemm wgt(const Ctx &c, Gemm g, int64_t off) {
 // 64 rows of W to fill its 512 places (with 64 of them, 256 x 256 of 16
 // blocks, it took 83 us against 44 for the two products); whole tiles, four
 // of them or more per block, since the bias is summed by the first four's
-// workgroups, 64 columns each; 16-byte accesses, and for the virtual X one
+// workgroups, 64 columns each; products that gemm() does not split over K (the
+// weight's is two slices at 1024 rows and fewer than 1024 inputs), since the
+// kernel adds all rows in one sum; 16-byte accesses, and for the virtual X one
 // position per wave and an embedding that fits beside the staged rows
 bool dense_ok(const TfShape &s, Gemm gd, Gemm gw, int nslots) {
   if ((int64_t)nslots * (gw.M / 64) < 512) return false;
   if (!s.bf16 || gd.K != kDN || gw.N != kDN || gw.ldc != kDN || gd.lda != kDN || gd.ldb != kDN || gw.M % 64) return false;
-  if (gw.M < kDN) return false;
+  if (gw.M < kDN || split_for(gd.M, gd.N, gd.K, gd.sPart) != 1 || split_for(gw.M + gw.aug, gw.N, gw.K, gw.sPart) != 1)
+    return false;
   if (gw.emb && (s.E % 16 || (size_t)s.V * (s.E + 8) * 2 + (size_t)kDChunk * 2 + 256 > 160 * 1024)) return false;
   set_vec(gd);
   set_vec(gw);

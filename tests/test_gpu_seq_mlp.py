@@ -208,6 +208,30 @@ def test_layers_of_few_inputs_match_general(gpu, hidden, t, k, opt, blocks):
     assert np.array_equal(gpu.decompress(blob).cpu().numpy(), a)
 
 
+@pytest.mark.parametrize("uneven", [False, True])
+def test_layers_of_1024_rows_match_general(gpu, uneven):
+    """1024 rows, where the weight product of a 256 x 256 layer is two slices
+    of 512 rows: the first and last of 130 blocks, of equal or of uneven
+    lengths (fewer than 128 of them in the last steps), equal their
+    single-block runs."""
+    bs, t, blocks = 1024, 2, 130
+    L = [t + 8 - (b % 4 if uneven else 0) for b in range(blocks)]
+    lens = [3 * bs * l for l in L]
+    cfg = model_small(t=t, E=64, hidden=[256, 256], bs=bs, optimizer="adam", lr=1e-2, precision="bf16",
+                      block_len=lens)
+    a = synth.generate(synth.Recipe(n=sum(lens), order=3, seed=52))
+    blob = gpu.compress(cfg, _cuda(a))
+    assert blob[5] == 7
+    got = cbf.parse(blob)["blocks"]
+    for b in (0, blocks - 1):
+        at = sum(lens[:b])
+        tok = gpu.encode_skmer(_cuda(a[at:at + lens[b]]), 3, 3)[:bs * L[b]]
+        c1 = {k: v for k, v in cfg.items() if k != "block_len"}
+        _, _, streams = gpu.model_trace(dict(c1, n_blocks=1), tok, streams=True)
+        assert b"".join(got[b]["streams"]) == streams
+    assert np.array_equal(gpu.decompress(blob).cpu().numpy(), a)
+
+
 @pytest.mark.parametrize("rows", [1, 16, 63, 64, 65, 127, 128])
 @pytest.mark.parametrize("t", [3, 16, 64])
 def test_first_layer_op_matches_general(gpu, rows, t):

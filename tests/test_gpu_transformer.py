@@ -232,11 +232,11 @@ def test_coding_rows_in_groups(gpu, bs, k):
     assert (P[0].double() - want).abs().max().item() <= 1e-6
 
 
-@pytest.mark.parametrize("A,F,heads,bs,blocks", [(256, 128, 4, 16, 256), (128, 256, 4, 16, 256)])
+@pytest.mark.parametrize("A,F,heads,bs,blocks", [(256, 128, 4, 16, 256), (128, 256, 4, 16, 256), (256, 256, 8, 1024, 130)])
 def test_wide_layers_match_general(gpu, A, F, heads, bs, blocks):
-    """256-wide layers of 128 inputs in enough blocks to fill 512 tiles of 64
-    rows: the first and last blocks' streams equal their single-block
-    runs."""
+    """256-wide layers of few inputs, and of 1024 rows, in enough blocks to
+    fill 512 tiles of 64 rows: the first and last blocks' streams equal
+    their single-block runs."""
     cfg = _tf(t=4, E=64, A=A, F=F, heads=heads, bs=bs, precision="bf16", optimizer="adam", lr=0.003, n_blocks=blocks)
     L = cfg["t"] + 8
     n1 = 3 * bs * L
