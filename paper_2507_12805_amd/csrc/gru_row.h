@@ -14,7 +14,10 @@
 //
 // Widths below the compiled ones (32 units, the padded input width) are
 // padded with zero weights: a padded term adds an exact zero, so every sum
-// keeps its value and its order (unit, then gate r, z, n).
+// keeps its value and its order (unit, then gate r, z, n).  A padded gate
+// row's input part and a padded unit's dh are set to zero, not summed: zero
+// weights times an infinite input would make them NaN, and they are factors
+// of the other units' padded terms.
 #pragma once
 #include "pmklc_internal.h"
 #include "seq_loop.h"
@@ -111,6 +114,7 @@ template <int NP>
 struct InputParts {
   float w[NP], b;
   int d, row, share, shares;
+  bool real;   // not a padded row
   __device__ __forceinline__ InputParts(const float *rows, const float *W, const int64_t (&bih)[2], int h) {
     shares = (int)blockDim.x / (2 * kG);
     const int item = (int)threadIdx.x % (2 * kG);
@@ -118,8 +122,9 @@ struct InputParts {
     d = item / kG;
     row = item % kG;
     const int gate = row / kU, u = row % kU;
+    real = u < h;
     load_row<NP>(rows, item, w);
-    b = u < h ? W[bih[d] + gate * h + u] : 0.0f;
+    b = real ? W[bih[d] + gate * h + u] : 0.0f;
   }
   template <class X>
   __device__ __forceinline__ void run(int t, X xat, float *pa) const {
@@ -128,7 +133,8 @@ struct InputParts {
       float x[NP];
 #pragma unroll
       for (int c = 0; c < NP; c += 4) lds_run<4>(xat(p, c), x + c);
-      pa[(d * t + p) * kG + row] = dot_in_order<NP>(b, w, x);
+      const float a = dot_in_order<NP>(b, w, x);
+      pa[(d * t + p) * kG + row] = real ? a : 0.0f;
     }
   }
 };

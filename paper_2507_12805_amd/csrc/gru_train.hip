@@ -570,7 +570,8 @@ __global__ __launch_bounds__(kRowT) __attribute__((amdgpu_waves_per_eu(2, 2))) v
         float x[kG];
         lds_run<2 * kU>(gs, x);
         lds_run<kU>(gh, x + 2 * kU);
-        dh += dot_in_order<kG>(0.0f, wc, x);
+        const float a = dot_in_order<kG>(0.0f, wc, x);
+        dh += u < h ? a : 0.0f;
       }
     }
   } else {

@@ -116,6 +116,23 @@ def test_shapes_fp32(gpu, orc, E, h, layers, t):
     assert np.abs(Pg.cpu().numpy() - Po).max() <= 1e-4
 
 
+@pytest.mark.parametrize("E,h,layers", [(16, 8, 1), (9, 31, 2), (16, 32, 1)])
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+def test_infinite_embedding(gpu, orc, E, h, layers, value):
+    """An infinite embedding value saturates the gates of the units there are
+    and touches no padding of narrower widths: within 1e-4 of the oracle."""
+    cfg = _cfg(precision="fp32", gru_layers=layers, static_E=E, gru_h=h)
+    ws = _static(orc, cfg)
+    ws[5 * E + 3] = value
+    tok = orc.encode_skmer(_dna(3 * 16 * 30 + 2, 34), 3, 3)
+    assert np.any(tok == 5)
+    steps = [8, 9, 29]
+    Pg, _ = gpu.model_trace(cfg, tok, steps=steps, static=ws)
+    Po, _, _ = orc.trace_block(cfg, tok, steps=steps, static=ws)
+    assert np.all(np.isfinite(Po))
+    assert np.abs(Pg.cpu().numpy() - Po).max() <= 1e-4
+
+
 def test_errors(gpu, orc):
     cfg = _cfg()
     ws = _static(orc, cfg)
