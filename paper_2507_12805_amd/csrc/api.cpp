@@ -7,7 +7,6 @@
 #include <chrono>
 #include <cmath>
 #include <cstdlib>
-#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <vector>
@@ -15,16 +14,13 @@
 #include "../../include/pmklc.h"
 #include "pmklc_internal.h"
 #include "seq_loop.h"
+#include "status_pool.h"
 
 using namespace pmklc;
 
-// Status words of the calls that take no workspace (the encoder's error flag,
-// the coder export's bit count and error flag): a fixed pool in device memory
-// owned by the library, 32 bytes per call in flight on a device, so that no
-// call allocates.  Each device holds its own copy (its address is looked up
-// once per device).
 namespace pmklc {
-constexpr int kStatusSlots = 64;
+// the status pool's words: each device holds its own copy (its address is
+// looked up once per device)
 __device__ __align__(256) unsigned long long g_status_words[kStatusSlots * 4];
 
 // The workspace of pmklc_compress_noalloc (callers that cannot allocate
@@ -37,59 +33,17 @@ __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 namespace {
 
-struct StatusPool {
-  std::mutex mu;
-  std::condition_variable cv;
-  unsigned long long *base = nullptr;   // this device's g_status_words
-  uint64_t busy = 0;                    // bit i: slot i in use
-};
 constexpr int kMaxDevices = 64;
 StatusPool g_status_pool[kMaxDevices];
 
-// One slot of the pool on the current device for the length of a call; a
-// call waits while all slots are taken.  A slot's words are zero when it is
-// acquired: the call that found them so after its stream drained says so
-// (clean), any other release drains the stream and clears them, so that no
-// kernel can still write a released slot.
-struct StatusSlot {
-  StatusPool *pool = nullptr;
-  hipStream_t st = nullptr;
-  int idx = -1;
-  unsigned long long *ptr = nullptr;   // 4 words of device memory
-  bool clean = false;                  // the stream has drained and the words are zero
-  hipError_t acquire(hipStream_t stream) {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    pool = &g_status_pool[dev];
-    std::unique_lock<std::mutex> lk(pool->mu);
-    if (!pool->base) {
-      void *p = nullptr;
-      e = hipGetSymbolAddress(&p, HIP_SYMBOL(pmklc::g_status_words));
-      if (e != hipSuccess) return e;
-      pool->base = static_cast<unsigned long long *>(p);
-    }
-    pool->cv.wait(lk, [&] { return pool->busy != ~0ull >> (64 - kStatusSlots); });
-    idx = __builtin_ctzll(~pool->busy);
-    pool->busy |= 1ull << idx;
-    ptr = pool->base + 4 * idx;
-    st = stream;
-    return hipSuccess;
-  }
-  ~StatusSlot() {
-    if (idx < 0) return;
-    if (!clean) {
-      (void)hipMemsetAsync(ptr, 0, 32, st);
-      (void)hipStreamSynchronize(st);
-    }
-    {
-      std::lock_guard<std::mutex> lk(pool->mu);
-      pool->busy &= ~(1ull << idx);
-    }
-    pool->cv.notify_one();
-  }
-};
+hipError_t acquire_status(StatusSlot &slot, hipStream_t st) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  return slot.acquire(g_status_pool[dev], st,
+                      [](void **p) { return hipGetSymbolAddress(p, HIP_SYMBOL(pmklc::g_status_words)); });
+}
 
 // numeric path of a container: which kernel computed its probabilities
 constexpr uint8_t kPathFP32Valu = 1, kPathBF16 = 2, kPathFP32Mfma = 3, kPathBF16Chip = 4, kPathTfBF16 = 5,
@@ -1169,7 +1123,7 @@ pmklc_status pmklc_encode_skmer(const uint8_t *bases_dev, uint64_t n, uint32_t s
   if (l && !tokens_dev) return PMKLC_ERR_INVALID_ARG;
   if (n == 0) { *n_tokens = 0; return PMKLC_OK; }
   StatusSlot slot;
-  HIP_TRY(slot.acquire(st));
+  HIP_TRY(acquire_status(slot, st));
   int *err = reinterpret_cast<int *>(slot.ptr);
   int herr = 0;
   hipError_t e = launch_skmer_direct(bases_dev, n, (int)s, (int)k, tokens_dev, l, err, st);
@@ -1923,7 +1877,7 @@ pmklc_status pmklc_wnc_encode(const uint32_t *cum_lo_dev, const uint32_t *cum_hi
   uint64_t need_words = (17 * m + 2 + 31) / 32;
   if (cap / 4 < need_words) { *nbits = 8 * need; return PMKLC_ERR_BUFFER_TOO_SMALL; }
   StatusSlot slot;
-  HIP_TRY(slot.acquire(st));
+  HIP_TRY(acquire_status(slot, st));
   uint64_t *nb_dev = reinterpret_cast<uint64_t *>(slot.ptr);
   int *err = reinterpret_cast<int *>(nb_dev + 1);
   uint64_t hb = 0;
