@@ -252,6 +252,46 @@ def test_first_layer_op_matches_general(gpu, rows, t):
     assert torch.equal(gpu.dm_backward(cfg, w, ctx, dl), gpu.dm_backward(cfg, buf[1:], ctx, dl))
 
 
+@pytest.mark.parametrize("t", [1, 3, 33])
+def test_embedding_gradient_matches_general(gpu, t):
+    """The embedding gradient of whole 32-row steps in registers (64 rows, t
+    odd) against the general product (63 rows: 63 t is no multiple of 32),
+    one slice at t 1 and 3, four of 576 rows at t 33. The 64th row's gradient
+    is zero, so that it adds exact zeros: equal bit for bit."""
+    import torch
+    cfg = model_small(t=t, E=64, hidden=[256, 256], bs=64, optimizer="adam", precision="bf16")
+    n = gpu.param_count(cfg)
+    g = torch.Generator(device="cuda").manual_seed(60 + t)
+    w = (torch.rand(n, generator=g, device="cuda") - 0.5) * 0.2
+    ctx = torch.randint(0, 64, (64, t), generator=g, device="cuda", dtype=torch.uint8)
+    dl = torch.randn((64, 64), generator=g, device="cuda")
+    dl[63] = 0
+    whole = gpu.dm_backward(cfg, w, ctx, dl)
+    assert whole[:64 * 64].abs().max().item() > 0
+    assert torch.equal(whole, gpu.dm_backward(cfg, w, ctx[:63].contiguous(), dl[:63].contiguous()))
+
+
+@pytest.mark.parametrize("rows", [1, 64, 130])
+def test_stored_gradient_matches_general(gpu, rows):
+    """A 256-wide layer of 32,768 inputs, from which on one slot's backward
+    streams its weights and stores its gradient (the virtual first layer, and
+    a hidden layer read from memory), against the general products, which
+    parameters off a 16-byte boundary take: equal bit for bit."""
+    import torch
+    for kw in (dict(t=512, E=64, hidden=[256]), dict(t=2, E=16, hidden=[32768, 256])):
+        cfg = model_small(bs=64, optimizer="adam", precision="bf16", **kw)
+        n = gpu.param_count(cfg)
+        g = torch.Generator(device="cuda").manual_seed(rows)
+        buf = torch.empty(n + 1, device="cuda")
+        w = ((torch.rand(n, generator=g, device="cuda") - 0.5) * 0.02).contiguous()
+        buf[1:] = w
+        ctx = torch.randint(0, 64, (rows, kw["t"]), generator=g, device="cuda", dtype=torch.uint8)
+        dl = torch.randn((rows, 64), generator=g, device="cuda")
+        assert w.data_ptr() % 16 == 0 and buf[1:].data_ptr() % 16 == 4
+        assert torch.equal(gpu.dm_forward(cfg, w, ctx), gpu.dm_forward(cfg, buf[1:], ctx))
+        assert torch.equal(gpu.dm_backward(cfg, w, ctx, dl), gpu.dm_backward(cfg, buf[1:], ctx, dl))
+
+
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
 @pytest.mark.parametrize("hidden,E,t,k", [([260, 132], 20, 7, 3), ([512, 388], 4, 3, 1), ([1024], 36, 33, 2)])
 @pytest.mark.parametrize("rows", [1, 3, 63, 65, 130])
