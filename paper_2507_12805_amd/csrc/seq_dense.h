@@ -333,7 +333,8 @@ __device__ __forceinline__ void dense_bias_store(const Gemm &gw, int slot, int D
 // 256 blocks of 4096 x 256, 128 rows: 1481 us (6.7 GB, 4.5 TB/s) against
 // 555 + 1330 us for the two products (without the loads ahead 1511; with all
 // of dOut in LDS and no barriers, one workgroup a CU, 1815); 16 blocks, 320
-// rows (571 MB): 154 us against 89 + 139 (without the loads ahead 206).
+// rows (571 MB): 154 us against 89 + 139 (without the loads ahead 206; 36
+// bytes a lane are spilled where the input is read from memory).
 template <bool VIRT, int EPI>
 __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(Gemm gd, Gemm gw, int V, int nslots) {
   extern __shared__ __align__(16) unsigned char raw[];

@@ -171,7 +171,7 @@ struct AttnLds {
 // Attention of rows [blockIdx.x rows, ...) of a slot (general form:
 // attn_fwd_kernel).  256 threads; thread = (head, position) for the scores
 // and probabilities, = column for the output; a head is half a wave, so
-// only the product is between barriers.  Two workgroups share a CU (78 KB
+// only the product is between barriers.  Two workgroups share a CU (73 KB
 // of LDS each).  Bound by the LDS and vector units (the product is 128
 // MFMAs a row): 36 us per step of 16 blocks of 320 rows, against 136 us for
 // the [k | v] product, 68 us for the attention and 37 us for the gather
@@ -338,7 +338,8 @@ __global__ __launch_bounds__(256, 2) void paper_kv_dx_kernel(TfShape s, const Tf
 // batch row's positions.  blockIdx.z: the keys' or the values' half, four
 // waves of 64 columns (two heads), all of E and the ones row: X^T passes
 // through LDS, d[k | v]^T is built in registers.  (Halves: 576 workgroups of
-// four waves are all resident at once; 288 of eight were 55 us, two rounds.)  45 us per step against 169 us for the product from memory.
+// four waves are all resident at once; 288 of eight were 55 us, two rounds.)
+// 46 us per step against 169 us for the product from memory.
 __global__ __launch_bounds__(256, 3) void paper_kv_dw_kernel(TfShape s, const TfState *st, const float *params,
                                                           const uint8_t *tokstep, int64_t sTok, const float *Q,
                                                           const float *dO, const float *att, const float *dS,

@@ -202,8 +202,9 @@ constexpr int kLdF = kCK + 1;           // FP32 LDS row (elements)
 constexpr int kPer = kBM * kCK / kGT;   // elements of each operand per thread and chunk (16)
 
 // Compiled for at least 4 waves per SIMD: at most 128 registers per lane
-// (vector and accumulation together, no spills), so that four workgroups
-// share a CU and hide each other's memory latency on grids of many blocks.
+// (vector and accumulation together, no spills), so that sixteen waves share
+// a CU and hide each other's memory latency on grids of many blocks: four
+// workgroups of 64 x 64 tiles, or two of 128 x 128 (66 KB of LDS each).
 template <bool BF16, bool TA, bool TB, int EPI, int ST, int BT>
 __global__ __launch_bounds__(4 * BT, 4) void gemm_kernel(Gemm g) {
   constexpr int kBM = BT, kBN = BT, kGT = 4 * BT;
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(4 * BT, 4) void gemm_kernel(Gemm g) {
   typedef typename std::conditional<BF16, __bf16, float>::type T;
   constexpr int LD = BF16 ? kLdB : kLdF;
   // the two operand tiles, and after the products the output tile (FP32,
-  // rows of 65) for a coalesced epilogue
+  // rows of kBN + 1) for a coalesced epilogue
   constexpr int kTile = (kBM + kBN) * LD * (int)sizeof(T);
   constexpr int kOut = kBM * (kBN + 1) * 4;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kTile > kOut ? kTile : kOut];
